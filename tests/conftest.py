@@ -35,7 +35,7 @@ def assert_models_close(got, ref, rel=REL_TOL, what="model", mask=None):
     rms = np.sqrt(np.mean(ref2 * ref2, axis=1, keepdims=True))
     scale = np.maximum(np.abs(ref2), rms)
     err = np.abs(got.reshape(ref2.shape) - ref2)
-    bad = err > rel * scale
+    bad = ~(err <= rel * scale)  # NaN is off, too
     if mask is not None:
         bad &= ~np.asarray(mask).reshape(ref2.shape)
     if bad.any():
