@@ -102,3 +102,39 @@ def test_captured_pass_replays(n, dim, S, B):
         assert torch.equal(captured.models(), eager.models())
     eager.close()
     captured.close()
+
+
+# one shape for each variant of the pass, with a last group that its rows do not fill
+@pytest.mark.parametrize("n,dim,S", [(3, 60, 5), (5, 200, 5), (130, 500, 5), (130, 1000, 3), (4, 600, 5), (4, 600, 37),
+                                     (33, 4097, 5), (130, 1500, 5), (130, 8190, 3), (130, 8200, 3)])
+@pytest.mark.parametrize("loss", ["logistic", "hinge"])
+def test_infinite_entry_stays_in_its_column(n, dim, S, loss):
+    """A step (B > S) from models with one infinite entry: its rows' margins are
+    infinite, which both losses have a derivative for, so the other columns stay
+    finite.  Rows that fill up a group but do not exist must not turn the
+    infinity into NaN (0 * inf) and add that to every column."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] infinite entry n={n} dim={dim} S={S} {loss}", flush=True)
+    wl = synth.DENSE_LR_32W.with_(n_workers=n, dim=dim, samples=S, batch=64, l2=0.0, loss=loss, lr_kind="const", lr0=0.1,
+                                  seed=n, scaled_frac=0.0)
+    p, i = oracle.graphs.ring(n)
+    X, y = synth.dense_data(wl)
+    W0 = synth.initial_models(wl) * np.float32(0.01)
+    hot = dim // 3
+    W0[:, hot] = np.where(np.arange(n) % 2, np.inf, -np.inf)
+    sess = asap.Session(n, dim, p, i, oracle.graphs.metropolis_weights(p, i))
+    sess.set_models(W0)
+    sess.bind_dense(X, y)
+    sess.local_sgd(asap.sgd_params(wl.loss, wl.lr_kind, wl.lr0, wl.l2, wl.batch, wl.seed))
+    assert sess.check()[0] == asap.OK
+    got = sess.models().cpu().numpy().copy()
+    sess.close()
+    with np.errstate(invalid="ignore"):  # the infinite column itself: inf - 0 * inf
+        ref = np.stack([oracle.sgd.sgd_pass_dense(W0[k].astype(np.float64), X[k], y[k],
+                                                  oracle.prng.schedule(S, wl.seed, k, 0), batch=wl.batch, loss=loss,
+                                                  lr_kind=wl.lr_kind, lr0=float(np.float32(wl.lr0)), l2=0.0, rnd=0)
+                        for k in range(n)])
+    rest = np.arange(dim) != hot
+    assert np.isfinite(ref[:, rest]).all()
+    assert_models_close(got[:, rest], ref[:, rest], what="finite columns")
