@@ -18,6 +18,7 @@ SHAPES = [
     (20, 1000, 101, 50, 0), (40, 1000, 24, 3, 0), (72, 700, 20, 20, 0),  # 8, 6 and 3 workgroups a worker at most
     (130, 500, 18, 5, 0), (130, 1023, 18, 5, 0),                         # one: two and four float4 a lane
     (300, 40, 30, 10, 0), (600, 300, 8, 8, 0), (1500, 70, 6, 4, 0),      # several workers a compute unit
+    (3072, 33, 5, 3, 0), (3073, 64, 4, 3, 0), (4096, 64, 5, 2, 0),       # ... 12 and 16: all resident in a launch
     (33, 4097, 20, 8, 0), (72, 9001, 9, 4, 0), (130, 1500, 16, 6, 0),    # several units a workgroup
     (130, 8190, 9, 4, 0), (66, 16384, 6, 3, 0),                          # ... of four float4 a lane
     (130, 8200, 6, 2, 0),                                                # wider than a workgroup's waves hold
