@@ -75,6 +75,42 @@ def test_dense_pass_shapes(n, dim, S, B, L):
     assert np.array_equal(got[0].view(np.uint32), got[1].view(np.uint32))
 
 
+@pytest.mark.parametrize("n,dim,fits", [(4096, 3, True), (4097, 64, False), (2048, 256, True), (1024, 512, True),
+                                         (1100, 300, False), (512, 1024, True), (520, 1000, False), (256, 2000, True),
+                                         (300, 1500, False), (256, 16384, True), (257, 9000, False)])
+def test_launch_fits_or_is_refused(n, dim, fits):
+    """The most workers a multi-round launch takes; one that does not fit is
+    refused with ASAP_E_STATE and leaves the state as it was."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] launch limit n={n} dim={dim}", flush=True)
+    wl = synth.DENSE_LR_32W.with_(n_workers=n, dim=dim, samples=2, batch=1, scaled_frac=0.0)
+    p, i = oracle.graphs.ring(n)
+    w = oracle.graphs.metropolis_weights(p, i)
+    gen = torch.Generator("cuda").manual_seed(n)
+    X = torch.randn((n, 2, (dim + 3) // 4 * 4), generator=gen, device="cuda")
+    y = torch.where(torch.rand((n, 2), generator=gen, device="cuda") < 0.5, -1.0, 1.0)
+    prm = asap.sgd_params(wl.loss, wl.lr_kind, wl.lr0, wl.l2, wl.batch, wl.seed)
+    stream, launch = asap.Session(n, dim, p, i, w), asap.Session(n, dim, p, i, w)
+    for s in (stream, launch):
+        asap.asap_bind_dense(s.ctx, X, y, 2, X.shape[2])
+        s.ready()
+    if fits:
+        launch.run_rounds(prm, 2, wait_ms=3000)
+    else:
+        with pytest.raises(asap.AsapError) as refused:
+            launch.run_rounds(prm, 2, wait_ms=3000)
+        assert refused.value.status == asap.E_STATE
+    for k in range(2):
+        stream.round(prm)
+        if not fits:
+            launch.round(prm)
+    assert stream.check()[0] == launch.check()[0] == asap.OK
+    assert torch.equal(stream.models(), launch.models())
+    stream.close()
+    launch.close()
+
+
 @pytest.mark.parametrize("n,dim,S,B", [(4, 600, 24, 64), (8, 2000, 64, 8)])  # one group a launch, eight
 def test_captured_pass_replays(n, dim, S, B):
     """A captured half-step replayed: every replay takes new exchange tags, so
