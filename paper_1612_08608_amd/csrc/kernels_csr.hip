@@ -420,9 +420,10 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
   }
 }
 
+// tid: threadIdx.x, as the caller has it (see rounds_csr_kernel).
 template <int E, bool PIPE>
-__device__ __forceinline__ void csr_pass(const SgdArgs& a, int i, Shared& sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void csr_pass(const SgdArgs& a, int i, Shared& sh, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
   const int sub = lane & (kRowLanes - 1);
   const int brow = wave * (64 / kRowLanes) + (lane / kRowLanes);  // fast-path row of this lane
   float* vrow = a.models + int64_t(i) * a.ld;
@@ -586,7 +587,7 @@ template <int E, bool PIPE>
 __global__ __launch_bounds__(kThreads) void sgd_csr_kernel(SgdArgs a) {
   if (a.run_if && *a.run_if == 0) return;  // the planned kernel took this round
   __shared__ Shared sh;
-  csr_pass<E, PIPE>(a, int(blockIdx.x), sh);
+  csr_pass<E, PIPE>(a, int(blockIdx.x), sh, int(threadIdx.x));
 }
 
 // Several rounds in one launch (rounds_device.h): one workgroup per worker
@@ -601,7 +602,14 @@ __global__ __launch_bounds__(kThreads) void rounds_csr_kernel(SgdArgs a, RoundsA
         rounds::fill_rowinfo(ra.seed, i, pass, a.S, a.row_ptr, a.y, ra.rowinfo + int64_t(i) * a.S);
       },
       [&](const SgdArgs& ar) {
-        csr_pass<E, PIPE>(ar, i, sh);
+        // Rows of more than 96 nonzeros: the pass's addresses are formed again
+        // every round; kept across rounds they were spilled (196 -> 144 bytes,
+        // four rounds of 64 x 2^20, 1024 rows of 83 nonzeros, B = 64: 4.58 ->
+        // 4.37 ms).  Shorter rows are better off with them kept (128 x 2^18,
+        // E = 6: 1.34 against 1.41 ms).
+        int tid = threadIdx.x;
+        if constexpr (E > 6) asm volatile("" : "+v"(tid));
+        csr_pass<E, PIPE>(ar, i, sh, tid);
         return true;
       });
 }
@@ -704,7 +712,7 @@ __global__ __launch_bounds__(kThreads) void rounds_csr_planned_kernel(SgdArgs a,
         if (__hip_atomic_load(pu.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
           // the general pass is one workgroup's: member 0 runs it alone
           ap.rowinfo = pu.rows_real;
-          if (m == 0) csr_pass<EG, true>(ap, i, sh.g);
+          if (m == 0) csr_pass<EG, true>(ap, i, sh.g, int(threadIdx.x));
           return true;
         }
         fast_pass<EF, MEM>(ap, pu, i, m, sh.f);
