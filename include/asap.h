@@ -284,7 +284,7 @@ asap_status asap_round(asap_ctx* ctx, const asap_sgd_params* p, void* stream);
  * pending); every worker has at most 64 in-neighbours and at most 64
  * out-neighbours (self included); rows of under 2^31 bytes; all workgroups
  * of the launch fit on the device at once, else ASAP_E_STATE (no round
- * runs and the state is as before).  Where a worker has several
+ * runs and the state is as before).  Where a dense worker has several
  * workgroups they always fit; with one per worker an MI355X holds 4096 dense
  * workers of dim <= 64, 2048 of dim <= 256, 1024 of dim <= 512, 512 of dim <=
  * 1024 and 256 wider ones, and 256 CSR workers.  `wait_ms` bounds each wait for a neighbour (0: 10 s).
