@@ -297,17 +297,13 @@ __global__ __launch_bounds__(1024) void mix_cols_kernel(MixArgs a, int nchunks) 
 __global__ __launch_bounds__(64) void mean_kernel(MixArgs a, uint32_t nseg) {
   const uint32_t seg = xcd_tile(blockIdx.x, nseg);
   const int lane = threadIdx.x;
-  int stale = 0;
-  for (int j = lane; j < a.n; j += 64) stale |= a.tag_src[j] != a.expect;
-  if (__ballot(stale) != 0ull) {
-    if (seg == 0)
-      for (int j = lane; j < a.n; j += 64) report_stale(a, j);
-    return;
-  }
   const int64_t c = int64_t(seg) * kSegFloats + lane * 4;
+  // nothing waits for the tags before the rows are loading (with few workers the
+  // wait was much of a wave's time: 1 x 2^24 48.4 -> 33.4 us, 3 x 2^24 147 -> 114)
+  const int64_t tag = a.tag_src[min(lane, a.n - 1)];
+  Acc4 acc;
   if (c < a.dim) {
     const double w0 = a.nbr_w[0];
-    Acc4 acc;
     // 32 rows' loads in flight per wave (one wave per segment leaves few
     // waves on a CU): 256 workers x 2^18 beside the next round's planning,
     // 0.32 -> 0.24 ms; the order of the sum is unchanged
@@ -317,6 +313,15 @@ __global__ __launch_bounds__(64) void mean_kernel(MixArgs a, uint32_t nseg) {
       if (a.scale) wt *= double(a.scale[j]);
       acc.fma(wt, *reinterpret_cast<const float4*>(a.src + int64_t(j) * a.ld + c));
     }
+  }
+  int stale = tag != a.expect;
+  for (int j = lane + 64; j < a.n; j += 64) stale |= a.tag_src[j] != a.expect;
+  if (__ballot(stale) != 0ull) {
+    if (seg == 0)
+      for (int j = lane; j < a.n; j += 64) report_stale(a, j);
+    return;
+  }
+  if (c < a.dim) {
     const float4 out = acc.round();
 #pragma unroll 4
     for (int j = 0; j < a.n; ++j) store_tail(a.dst + int64_t(j) * a.ld + c, out, c, a.dim);
