@@ -167,7 +167,8 @@ __device__ __forceinline__ void lds_barrier() {
 // Column kernel: any graph of up to 1024 workers that the slab kernel does not
 // take.  A block walks a contiguous range of column chunks; a chunk is all n
 // rows of 4 LPR columns (LPR lanes of a float4 each per row: 64 up to 128
-// rows, then 32, 16, 8, so that a chunk is at most 128 KiB), staged in LDS, so
+// rows, then 32, 16, 8, so that a chunk is at most 128 KiB, and fewer where
+// there are few columns, see launch_mix_cols), staged in LDS, so
 // every model byte crosses HBM once and a neighbour is an LDS read.  Thread t
 // stages and computes float4 slots t + T m of the chunk (m < PF): slot s is
 // float4 s mod LPR of row s div LPR.  The loads of the next chunk are in
@@ -778,11 +779,13 @@ hipError_t launch_mix_slab(const MixArgs& a, int max_deg, int n_cu, hipStream_t 
   return launch_slab<17>(a, n_cu, s);
 }
 
-// Column kernel when there are at most 1024 rows (hipErrorNotSupported
-// otherwise).  Lanes per row: the most that keep a chunk within 128 KiB.
 // Threads for about four slots each, 64 to 1024; blocks per compute unit as LDS
 // and threads allow.
 constexpr size_t kColsLds = (160 << 10) - 512;  // of a compute unit's 160 KiB, beside the verdicts
+size_t cols_lds(const MixArgs& a, int lanes, int64_t nnz) {
+  const size_t lists = lanes < 64 ? size_t(nnz) * 6 + size_t(a.n) * (a.scale ? 6 : 2) + 16 : 0;
+  return size_t(a.n) * size_t(lanes) * 16 + lists;
+}
 template <int LPR>
 hipError_t launch_cols(const MixArgs& a, int64_t nnz, int n_cu, hipStream_t s) {
   const int slots = a.n * LPR, C = 4 * LPR;
@@ -791,7 +794,7 @@ hipError_t launch_cols(const MixArgs& a, int64_t nnz, int n_cu, hipStream_t s) {
   int T = 64;
   while (T < 1024 && T * 4 < slots) T *= 2;
   const int pf = (slots + T - 1) / T;  // <= 8
-  const size_t lists = LPR < 64 ? size_t(nnz) * 6 + size_t(a.n) * (a.scale ? 6 : 2) + 16 : 0, lds = size_t(slots) * 16 + lists;
+  const size_t lds = cols_lds(a, LPR, nnz);
   if (lds > kColsLds || nnz > 65535) return hipErrorNotSupported;
   const int per_cu = int(std::max<size_t>(1, std::min<size_t>((size_t(160) << 10) / (lds + 256), size_t(1024 / T))));
   const dim3 g(uint32_t(std::min<int64_t>(chunks, int64_t(per_cu) * n_cu))), b(static_cast<uint32_t>(T));
@@ -808,11 +811,30 @@ hipError_t launch_cols(const MixArgs& a, int64_t nnz, int n_cu, hipStream_t s) {
   return go(mix_cols_kernel<LPR, 8>);
 }
 
+// Column kernel when there are at most 1024 rows (hipErrorNotSupported
+// otherwise).  Lanes per row: the most that keep a chunk within 128 KiB.
 hipError_t launch_mix_cols(const MixArgs& a, int64_t nnz, int n_cu, hipStream_t s) {
   if (a.n > kColsMaxRows) return hipErrorNotSupported;
-  if (a.n <= 128) return launch_cols<64>(a, nnz, n_cu, s);
-  if (a.n <= 256) return launch_cols<32>(a, nnz, n_cu, s);
-  if (a.n <= 512) return launch_cols<16>(a, nnz, n_cu, s);
+  const int most = a.n <= 128 ? 64 : a.n <= 256 ? 32 : a.n <= 512 ? 16 : 8;
+  int lanes = most;
+  // Above 64 rows a block has 1024 threads and takes all rows of a chunk one
+  // after the other, so models with fewer chunks than compute units get
+  // narrower ones (tile kernel / most lanes / this, us a reduce): 100 x 4096,
+  // 8 neighbours 12.8 / 16.2 / 9.4; 128 x 4096, 64 neighbours 54 / 84 / 37;
+  // 200 x 4096, 16 neighbours 19.2 / 25.1 / 14.1.
+  auto chunks = [&](int l) { return (a.dim + 4 * l - 1) / (4 * l); };
+  if (a.n > 64)
+    while (lanes > 8 && chunks(lanes) < n_cu) lanes /= 2;
+  if (cols_lds(a, lanes, nnz) > kColsLds) lanes = most;
+  // With 8 lanes there are no narrower ones, and few blocks for many rows are
+  // slower than the tile kernel: 1000 x 4096, 4 neighbours 16.3 and 20.8 us,
+  // 800 x 1000 12.7 and 15.2, 576 x 1000, 16 neighbours, 21.5 and 22.4; 520 x
+  // 1000, 4 neighbours, 14.6 and 10.9.  With a chunk for every compute unit the
+  // column kernel is ahead (1000 x 16384, 4 neighbours, 45 and 39).
+  if (a.n > 544 && chunks(lanes) < n_cu) return hipErrorNotSupported;
+  if (lanes == 64) return launch_cols<64>(a, nnz, n_cu, s);
+  if (lanes == 32) return launch_cols<32>(a, nnz, n_cu, s);
+  if (lanes == 16) return launch_cols<16>(a, nnz, n_cu, s);
   return launch_cols<8>(a, nnz, n_cu, s);
 }
 

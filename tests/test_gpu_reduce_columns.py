@@ -1,6 +1,6 @@
-"""The reduce's column kernel at the edges of its layouts: worker counts around
-a change of lanes per row, graphs whose lists just fit or do not fit beside the
-chunk, ragged columns, rows with a stale neighbour."""
+"""The reduce's column kernel at the edges of its layouts: worker counts and
+widths around a change of lanes per row, graphs whose lists just fit or do not
+fit beside the chunk, ragged columns, rows with a stale neighbour."""
 import numpy as np
 import pytest
 
@@ -20,10 +20,20 @@ def _rows_in_order(W, ptr, idx, w):
     return out.astype(np.float32)
 
 
+def _circulant(n, d):
+    """Every worker with its d nearest and itself."""
+    rows = [sorted({(i + s) % n for s in range(-(d // 2), d // 2 + 1)}) for i in range(n)]
+    return np.arange(n + 1, dtype=np.int32) * (d + 1), np.concatenate(rows).astype(np.int32)
+
+
 SHAPES = [
     (1, 0, 5), (3, 2, 1), (5, 2, 255), (7, 4, 256), (9, 2, 257), (25, 4, 1023), (66, 6, 515), (127, 4, 1030),
     (128, 20, 260), (129, 4, 131), (254, 18, 127), (255, 4, 128), (257, 4, 65), (511, 6, 64), (513, 4, 33),
     (1000, 4, 70), (1000, 16, 67), (1023, 4, 31), (1026, 2, 40),
+    # a chunk for every compute unit, with each number of lanes; narrower ones;
+    # lists that do not fit beside a narrower one
+    (66, 4, 65281), (128, 20, 65537), (254, 6, 32641), (400, 4, 16321), (544, 4, 8100), (545, 4, 8100), (1000, 4, 8161),
+    (100, 6, 40003), (255, 4, 20000), (300, 20, 9001), (127, 124, 40001), (128, 126, 20003),
 ]
 
 
@@ -35,7 +45,7 @@ def test_reduce_is_the_rows_sum_in_order(n, d, dim):
     if n == 1:
         p, i = np.array([0, 1], np.int32), np.zeros(1, np.int32)
     else:
-        p, i = oracle.graphs.random_regular(n, d, 3)
+        p, i = oracle.graphs.random_regular(n, d, 3) if d <= 20 else _circulant(n, d)
     w = oracle.graphs.metropolis_weights(p, i)
     W = np.random.default_rng([n, dim]).standard_normal((n, dim), dtype=np.float32)
     sess = asap.Session(n, dim, p, i, w)
