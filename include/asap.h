@@ -188,7 +188,9 @@ asap_status asap_bind_models(asap_ctx* ctx, float* buf0, float* buf1, int64_t ld
 /* Bind dense shards: X [n][samples][ldx] fp32 (ldx >= dim, multiple of 4,
  * 16-byte aligned), y [n][samples] fp32 in {-1, +1}; worker i owns
  * X[i], y[i].  dim <= 16384 on this path.  samples >= 1.  Entries of X past
- * dim are never used.  For dim > 256 a pass may use several workgroups per
+ * dim are never used.  For dim in (1024, 8192] the next asap_bind_workspace
+ * rejects labels outside {-1, +1} and features that are not finite with
+ * ASAP_E_INVALID_ARG; other widths are taken as they are.  For dim > 256 a pass may use several workgroups per
  * worker, each with a part of the columns, that exchange the minibatch's
  * partial margins (a cooperative launch); the workspace holds those. */
 asap_status asap_bind_dense(asap_ctx* ctx, const float* X, const float* y,

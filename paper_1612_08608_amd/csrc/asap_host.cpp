@@ -877,11 +877,10 @@ extern "C" asap_status asap_bind_workspace(asap_ctx* c, void* dev, size_t bytes,
        (e = launch_fill_i32(at<int32_t>(c, c->off_dtag), int64_t(n), 1, s))))
     return hip_fail(c, e, "member exchange init");
   if (c->kind == kDense && c->dim > 1024 && c->dim <= 8192) {
-    // labels and finiteness
+    // labels and finiteness, at the widths that asap_bind_dense names
     int64_t* scan = at<int64_t>(c, c->off_scan);
-    if ((e = launch_fill_i64(scan, 8, 0, s)) || (e = launch_fill_f32(at<float>(c, c->off_vmax), c->n, 0.0f, s)) ||
-        (e = launch_dense_scan(c->X, c->y, c->n, c->S, c->dim, c->ldx, at<float>(c, c->off_vmax),
-                               reinterpret_cast<unsigned long long*>(scan), s)))
+    if ((e = launch_fill_i64(scan, 8, 0, s)) ||
+        (e = launch_dense_scan(c->X, c->y, c->n, c->S, c->dim, c->ldx, reinterpret_cast<unsigned long long*>(scan), s)))
       return hip_fail(c, e, "dense scan");
     int64_t h[2];
     if ((e = hipMemcpyAsync(h, scan, sizeof h, hipMemcpyDeviceToHost, s)) || (e = hipStreamSynchronize(s)))

@@ -228,7 +228,7 @@ hipError_t launch_rounds_csr_planned(const SgdArgs& a, const RoundsArgs& ra, con
 bool mix_slab_applies(const MixArgs& a, int max_deg);
 
 hipError_t launch_dense_scan(const float* X, const float* y, int32_t n, int64_t S, int64_t dim, int64_t ldx,
-                             float* xmax, unsigned long long* out, hipStream_t s);
+                             unsigned long long* out, hipStream_t s);
 DenseShape dense_shape(int64_t n, int64_t dim, int32_t batch, int64_t samples, int n_cu);
 size_t dense_xch_bytes(int64_t n, int64_t dim);  // exchange words of one worker, at most (0: never several members)
 hipError_t launch_sgd_dense_slices(const SgdArgs& a, const DenseSync& ds, hipStream_t s);

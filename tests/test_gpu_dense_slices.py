@@ -175,3 +175,38 @@ def test_infinite_entry_stays_in_its_column(n, dim, S, loss):
     rest = np.arange(dim) != hot
     assert np.isfinite(ref[:, rest]).all()
     assert_models_close(got[:, rest], ref[:, rest], what="finite columns")
+
+
+@pytest.mark.parametrize("dim,checked", [(1024, False), (1025, True), (8192, True), (8193, False)])
+def test_shards_checked_when_bound(dim, checked):
+    """Widths at which labels and finiteness are checked; padding columns are
+    not."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] bind check dim={dim}", flush=True)
+    p, i = oracle.graphs.ring(3)
+    ldx = (dim + 3) // 4 * 4 + 4
+
+    def bind(edit):
+        X, y = torch.ones((3, 20, ldx), device="cuda"), torch.ones((3, 20), device="cuda")
+        X[:, :, dim:] = float("nan")
+        edit(X, y)
+        sess = asap.Session(3, dim, p, i, oracle.graphs.metropolis_weights(p, i))
+        asap.asap_bind_dense(sess.ctx, X, y, 20, ldx)
+        sess.ready()
+        sess.close()
+
+    def label(X, y):
+        y[2, 19] = 0.5
+
+    def value(X, y):
+        X[2, 19, dim - 1] = float("inf")
+
+    bind(lambda X, y: None)
+    for edit in (label, value):
+        if checked:
+            with pytest.raises(asap.AsapError) as refused:
+                bind(edit)
+            assert refused.value.status == asap.E_INVALID_ARG
+        else:
+            bind(edit)
