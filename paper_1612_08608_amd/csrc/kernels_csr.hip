@@ -217,8 +217,8 @@ static_assert(kBMax <= kThreads, "one row per thread");
 // trips for each cold nonzero).
 // U: nonzeros of a lane loaded together.
 template <int U>
-__device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, const RowInfo* ri, int Bp, float* vrow,
-                                             Shared& sh, int H, double s, double coefA, double to_fx, double from_fx) {
+__device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, const RowInfo* ri, int Bp, Shared& sh,
+                                             int H, double s, double coefA, double to_fx, double from_fx) {
   GenShared& g = *reinterpret_cast<GenShared*>(sh.cold);
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // keeps this step's addresses from being held across the pass
@@ -536,7 +536,7 @@ __device__ __forceinline__ void csr_pass(const SgdArgs& a, int i, Shared& sh, in
       for (int q = tid; q < kCold; q += kThreads) prev.key[q] = kEmpty;
       if (tid == 0) sh.stats[st][0] = sh.stats[st][1] = 0;
     } else {
-      general_step<PIPE ? 2 : 6>(a, w, ri + b0, Bp, vrow, sh, H, s, coefA, to_fx, from_fx);
+      general_step<PIPE ? 2 : 6>(a, w, ri + b0, Bp, sh, H, s, coefA, to_fx, from_fx);
       if (tid == 0) sh.stats[st][0] = sh.stats[st][1] = 0;
       if (PIPE) {
         // the tables as a fast step expects them (general_step leaves the
