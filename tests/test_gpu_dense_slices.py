@@ -24,6 +24,8 @@ SHAPES = [
     (130, 8200, 6, 2, 0),                                                # wider than a workgroup's waves hold
     (1, 8193, 12, 5, 0), (2, 16381, 10, 64, 0),                          # few workers, wide models, batch > samples
     (4, 600, 48, 8, 2), (12, 2000, 40, 10, 1),                           # several rounds a pass
+    # groups of eight rows (more than 32 rows a step): five to eight units, several groups a step
+    (8, 2048, 150, 128, 0), (12, 1300, 70, 40, 0), (5, 700, 200, 130, 0), (16, 2000, 300, 256, 0), (3, 1793, 90, 66, 1),
 ]
 
 
@@ -210,3 +212,96 @@ def test_shards_checked_when_bound(dim, checked):
             assert refused.value.status == asap.E_INVALID_ARG
         else:
             bind(edit)
+
+
+def _two_sessions(torch, shapes):
+    """Dense sessions on random shards, with their parameters."""
+    out = []
+    for k, (n, dim, S, B) in enumerate(shapes):
+        p, i = oracle.graphs.ring(n)
+        gen = torch.Generator("cuda").manual_seed(k)
+        X = torch.randn((n, S, (dim + 3) // 4 * 4), generator=gen, device="cuda")
+        y = torch.where(torch.rand((n, S), generator=gen, device="cuda") < 0.5, -1.0, 1.0)
+        sess = asap.Session(n, dim, p, i, oracle.graphs.metropolis_weights(p, i))
+        asap.asap_bind_dense(sess.ctx, X, y, S, X.shape[2])
+        sess.ready()
+        out.append((sess, asap.sgd_params("logistic", "inv_sqrt", 0.1, 0.0, B, k), X, y))
+    torch.cuda.synchronize()
+    return out
+
+
+STREAM_PAIRS = [((25, 1000, 400, 50), (33, 1000, 300, 20)), ((20, 600, 300, 16), (12, 12000, 64, 16)),
+                ((32, 4096, 128, 32), (64, 1000, 256, 32))]
+
+
+@pytest.mark.parametrize("pair", STREAM_PAIRS)
+def test_two_contexts_on_two_streams(pair):
+    """Passes whose workgroups wait for each other, of two contexts at once:
+    each context's bits are those it has alone."""
+    import threading
+
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] two contexts {pair}", flush=True)
+    rounds = 20
+    want = []
+    for sess, prm, *_ in _two_sessions(torch, pair):
+        for _ in range(rounds):
+            sess.round(prm)
+        assert sess.check()[0] == asap.OK
+        want.append(sess.models().clone())
+        sess.close()
+    both = _two_sessions(torch, pair)
+
+    def work(sess, prm):
+        stream = torch.cuda.Stream()
+        for _ in range(rounds // 2):
+            sess.round(prm, stream=stream)
+        sess.run_rounds(prm, rounds // 2, wait_ms=3000, stream=stream)
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=both[k][:2]) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in range(2):
+        assert both[k][0].check()[0] == asap.OK
+        assert torch.equal(both[k][0].models(), want[k])
+        both[k][0].close()
+
+
+@pytest.mark.parametrize("pair", STREAM_PAIRS)
+def test_two_captured_passes_on_two_streams(pair):
+    """The same for captured half-steps, replayed side by side: together they
+    have more workgroups than fit, and each launch has to get all of its own."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] two captured passes {pair}", flush=True)
+    replays = 10
+    want = []
+    for sess, prm, *_ in _two_sessions(torch, pair):
+        for _ in range(replays):
+            sess.local_sgd(prm)
+            asap.asap_set_round(sess.ctx, 0, 0)
+        assert sess.check()[0] == asap.OK
+        want.append(sess.models().clone())
+        sess.close()
+    both = _two_sessions(torch, pair)
+    graphs, streams = [], []
+    for sess, prm, *_ in both:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            sess.local_sgd(prm)
+        graphs.append(g)
+        streams.append(torch.cuda.Stream())
+    torch.cuda.synchronize()
+    for _ in range(replays):
+        for g, stream in zip(graphs, streams):
+            with torch.cuda.stream(stream):
+                g.replay()
+    torch.cuda.synchronize()
+    for k in range(2):
+        assert both[k][0].check()[0] == asap.OK
+        assert torch.equal(both[k][0].models(), want[k])
+        both[k][0].close()

@@ -193,13 +193,13 @@ def test_dense_shapes(torch, n, dim, S, B, l2):
     _free_run(torch, wl, "complete", 0, 3, W0=W0)
 
 
-# dim in (1024, 8192] takes the wide dense kernel: several workgroups per
-# worker (up to 8) split every minibatch and meet once per step
+# wide dense models: a worker's workgroups own columns and exchange the
+# minibatch's partial margins
 @pytest.mark.parametrize("n,dim,S,B,l2,loss", [
-    (3, 1025, 40, 5, 0.0, "logistic"),    # one float4 per thread, ragged dim, B < members
+    (3, 1025, 40, 5, 0.0, "logistic"),    # five units, the last of one column
     (2, 2048, 33, 8, 0.05, "logistic"),   # ragged last minibatch, L2
-    (6, 3001, 100, 16, 0.0, "hinge"),     # two float4 per thread, hinge
-    (2, 8192, 24, 3, 0.0, "logistic"),    # four float4 per thread, B < members
+    (6, 3001, 100, 16, 0.0, "hinge"),     # twelve units, ragged, hinge
+    (2, 8192, 24, 3, 0.0, "logistic"),    # 32 units, fewer rows a step than row waves
     (300, 1500, 16, 4, 0.0, "logistic"),  # more workers than compute units: one workgroup each
 ])
 def test_dense_wide_kernel_shapes(torch, n, dim, S, B, l2, loss):

@@ -69,3 +69,36 @@ def test_reduce_is_the_rows_sum_in_order(n, d, dim):
     assert (st, bad) == (asap.E_EPOCH, min(readers))
     assert np.array_equal(sess.models().cpu().numpy().view(np.uint32), want.view(np.uint32))
     sess.close()
+
+
+@pytest.mark.parametrize("n,d,dim", [(100, 4, 70001), (300, 6, 20001), (1000, 4, 9001), (1000, 4, 300), (64, 0, 5003),
+                                     (64, 8, 9000), (64, 16, 9000), (1030, 4, 500)])
+def test_captured_reduce_replays(n, d, dim):
+    """Every kernel of the reduce captured and replayed on other models, with
+    eager work between the replays (d = 0: the complete graph)."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[gpu] captured reduce n={n} d={d} dim={dim}", flush=True)
+    p, i = oracle.graphs.random_regular(n, d, 5) if d else oracle.graphs.complete(n)
+    w = oracle.graphs.metropolis_weights(p, i)
+    gen = torch.Generator("cuda").manual_seed(n)
+    eager, captured = asap.Session(n, dim, p, i, w), asap.Session(n, dim, p, i, w)
+    for s in (eager, captured):
+        s.ready()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        captured.stochastic_reduce()
+    for _ in range(4):
+        W = torch.randn((n, dim), generator=gen, device="cuda")
+        for s in (eager, captured):
+            asap.asap_set_round(s.ctx, 0, 0)
+            s.bufs[0][:, :dim].copy_(W)
+            s.bufs[1].zero_()
+        eager.stochastic_reduce()
+        g.replay()
+        torch.cuda.synchronize()
+        assert eager.check()[0] == captured.check()[0] == asap.OK
+        assert bool(eager.bufs[1].any()) and torch.equal(eager.bufs[1], captured.bufs[1])
+    eager.close()
+    captured.close()
