@@ -207,9 +207,9 @@ static_assert(kBMax <= kThreads, "one row per thread");
 
 // One step of any shape: Bp <= 512 rows of any length.  Bound by the latency
 // of its phases, so every phase keeps all lanes busy and nothing is read
-// serially: row descriptors go to LDS once; margins take 16 lanes a row, 64
-// rows at a time, with nonzeros loading two segments ahead and model entries
-// one; rows are cut into chunks by their cold nonzeros (counted with the
+// serially: row descriptors go to LDS once; margins take 16 lanes a row or
+// more, 64 rows at a time, with nonzeros loading two segments ahead and model
+// entries one; rows are cut into chunks by their cold nonzeros (counted with the
 // margins), so that most steps are one or two chunks.  With one wave a row,
 // descriptors re-read from memory by every thread and chunks of 1024 nonzeros
 // of any kind, 16 workers x 4000 rows of 75 nonzeros, B = 200, took 93 us a
@@ -222,8 +222,11 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
   GenShared& g = *reinterpret_cast<GenShared*>(sh.cold);
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // keeps this step's addresses from being held across the pass
-  const int lane = tid & 63, wave = tid >> 6, sub = lane & (kRowLanes - 1);
-  const int grp = wave * (64 / kRowLanes) + lane / kRowLanes;  // 64 groups of 16 lanes
+  const int lane = tid & 63, wave = tid >> 6;
+  // Lanes of a row: 16, and more where rows are so few that groups would be
+  // idle (64 x 1029, B = 8, 600 draws a row: 1.38 ms a round with 16, 0.97 so)
+  const int rls = Bp <= kWaves ? 6 : Bp <= 2 * kWaves ? 5 : 4, rl = 1 << rls;
+  const int sub = tid & (rl - 1), grp = tid >> rls, groups = kThreads >> rls;
   __syncthreads();  // the previous step's tables are no longer read
   for (int q = tid; q < kGenSlots; q += kThreads) {
     g.key[q] = kEmpty;
@@ -237,8 +240,8 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
   }
   __syncthreads();
 
-  // Each group of lanes walks segments of 16 U nonzeros of its rows (row b,
-  // entries from e0 on; lane sub has entries e0 + sub + 16 u).
+  // Each group of lanes walks segments of rl U nonzeros of its rows (row b,
+  // entries from e0 on; lane sub has entries e0 + sub + rl u).
   struct Seg {
     int code[U];
     float val[U], v[U];
@@ -246,9 +249,9 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
   };
   // the segment after (b, e0), of rows below `end`
   auto next = [&](int& b, int& e0, int end) {
-    e0 += kRowLanes * U;
+    e0 += U << rls;
     if (b >= end || e0 >= g.len[b]) {
-      b += 64;
+      b += groups;
       e0 = 0;
     }
   };
@@ -259,7 +262,7 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
     const uint32_t st = b < end ? uint32_t(g.start[b]) : 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + sub + kRowLanes * u;
+      const int e = e0 + sub + (u << rls);
       const uint32_t off = e < len ? (st + uint32_t(e)) * 4u : 0xffffffffu;  // past the end: 0
       x.code[u] = ld_i32(w.code, off);
       x.val[u] = ld_f32(w.val, off);
@@ -269,7 +272,7 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
     const int len = x.b < end ? g.len[x.b] : 0;
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (x.e0 + sub + kRowLanes * u >= len) x.code[u] = -1;
+      if (x.e0 + sub + (u << rls) >= len) x.code[u] = -1;
   };
 
   // Margins, coefficients and cold nonzeros per row: while one segment is
@@ -304,8 +307,16 @@ __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, c
         cold += x.code[u] >= 0;
       }
       if (x.b != xn.b) {  // the row's last segment
-        const double dot = row16_sum(part);
-        const int rc = row16_sum_i(cold);
+        double dot = row16_sum(part);
+        int rc = row16_sum_i(cold);
+        if (rls > 4) {
+          dot += __shfl_xor(dot, 16, 64);
+          rc += __shfl_xor(rc, 16, 64);
+        }
+        if (rls > 5) {
+          dot += __shfl_xor(dot, 32, 64);
+          rc += __shfl_xor(rc, 32, 64);
+        }
         if (sub == 0) {
           g.coef[x.b] = loss_coef(s * dot, double(g.y[x.b]), a.loss);
           g.cold[x.b] = rc;

@@ -17,6 +17,9 @@ SHAPES = [
     (2, 200000, 40, 20, 100, 700, 1e-3),      # long rows in small minibatches
     (1, 150000, 9, 4, 4000, 4096, 0.0),       # rows that fill the table
     (2, 150000, 513, 512, 0, 12, 1e-3),       # the largest minibatch, a last one of one row, empty rows
+    # 64, 32 and 16 lanes a row: 16 rows and one more, 32 and one more
+    (2, 30000, 48, 16, 120, 400, 1e-3), (2, 30000, 50, 17, 0, 500, 0.0), (2, 2000, 64, 32, 129, 300, 0.0),
+    (3, 30000, 66, 33, 1, 200, 0.0), (2, 100000, 22, 10, 1000, 4096, 0.0),
 ]
 
 
