@@ -299,10 +299,15 @@ __device__ void drive(SgdArgs a, const RoundsArgs& ra, int i, int member, int me
     if constexpr (THROUGH) store_done();
     else __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    bool parts = true;
+    if (members > 1 && member == 0 && tid < 64) {  // lane q waits for member q (at most 32)
+      if (tid > 0 && tid < members) parts = wait_tag(ms + 1 + tid, tag_half(r), wall_clock64() + ra.wait_ticks);
+      parts = __all(parts);
+    }
     if (tid == 0) {
       const long long deadline = wall_clock64() + ra.wait_ticks;
       if (member == 0) {
-        for (int q = 1; q < members && !stop; ++q) stop = !wait_tag(ms + 1 + q, tag_half(r), deadline);
+        stop = !parts;
         if (members > 1) acquire_fence();  // the others' parts, before the next pass reads the row
         if (stop) report_stale(ra.err, i);
         else if constexpr (THROUGH) tag_store(tn + i, tag_start(r + 1));
