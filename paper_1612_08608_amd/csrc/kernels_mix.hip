@@ -19,10 +19,11 @@
 // groups of 8 lanes (DPP) so that each store writes a whole 128-byte line of
 // a row rather than 16 bytes in each of 64 rows.
 //
-// column kernel (every other graph of up to 1024 workers): a workgroup takes
-// all n rows of a narrow column range through LDS, see mix_cols_kernel.
+// column kernel (other graphs of up to 1024 workers, but for the sizes that
+// launch_mix_cols names): a workgroup takes all n rows of a narrow column range
+// through LDS, see mix_cols_kernel.
 //
-// tile kernel (n above 1024): a tile is one 1 KiB segment of 16 consecutive output
+// tile kernel (n above 1024 and what the column kernel leaves): a tile is one 1 KiB segment of 16 consecutive output
 // rows, one wave per row segment with 16-byte loads; the tiles of one column
 // range go to one XCD so that re-reads of a neighbour's segment hit its L2.
 //
@@ -832,6 +833,22 @@ hipError_t launch_mix_cols(const MixArgs& a, int64_t nnz, int n_cu, hipStream_t 
   // 1000, 4 neighbours, 14.6 and 10.9.  With a chunk for every compute unit the
   // column kernel is ahead (1000 x 16384, 4 neighbours, 45 and 39).
   if (a.n > 544 && chunks(lanes) < n_cu) return hipErrorNotSupported;
+  // Rows of up to three entries whose models stay in the memory-side cache
+  // (256 MB): the tile kernel's second and third read of a row cost little, and
+  // it has no chunk to stage first and no last round of chunks that fills the
+  // device in part.  Both buffers of 105 to 260 MB, from 48 MB above 128 workers
+  // (tile / column kernel, chain and ring, us): 100 x 200000 34.0 / 47.7 and
+  // 39.6 / 48.0; 200 x 33000 15.7 / 19.5 and 17.7 / 20.3; 500 x 33000 30.9 /
+  // 41.6 and 35.5 / 42.4.  Below, 100 x 131072 24.3 / 22.4 and 28.0 / 22.5;
+  // above, 500 x 65536 76.9 / 62.3 and 84.4 / 63.7; five entries, 100 x 200000
+  // 71.0 / 51.5.
+  // From 40 MB where the last round of chunks leaves more than 30% of all
+  // rounds idle: 100 x 80000 17.3 / 20.3 and 19.6 / 20.6, 160 x 33000 14.2 / 16.3.
+  const int64_t both = 8 * int64_t(a.n) * a.dim, rounds = (chunks(lanes) + n_cu - 1) / n_cu;
+  const bool uneven = 10 * chunks(lanes) < 7 * rounds * n_cu;
+  if (a.n > 64 && nnz <= 3 * int64_t(a.n) && both <= 260000000 &&
+      both >= (uneven ? 40000000 : a.n > 128 ? 48000000 : 105000000))
+    return hipErrorNotSupported;
   if (lanes == 64) return launch_cols<64>(a, nnz, n_cu, s);
   if (lanes == 32) return launch_cols<32>(a, nnz, n_cu, s);
   if (lanes == 16) return launch_cols<16>(a, nnz, n_cu, s);

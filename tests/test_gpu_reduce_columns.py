@@ -34,6 +34,8 @@ SHAPES = [
     # lists that do not fit beside a narrower one
     (66, 4, 65281), (128, 20, 65537), (254, 6, 32641), (400, 4, 16321), (544, 4, 8100), (545, 4, 8100), (1000, 4, 8161),
     (100, 6, 40003), (255, 4, 20000), (300, 20, 9001), (127, 124, 40001), (128, 126, 20003),
+    # rows of three entries, models within the memory-side cache and below
+    (66, 2, 198900), (66, 2, 198800), (129, 2, 46600), (129, 2, 46400),
 ]
 
 
