@@ -213,8 +213,8 @@ static_assert(kBMax <= kThreads, "one row per thread");
 // margins), so that most steps are one or two chunks.  With one wave a row,
 // descriptors re-read from memory by every thread and chunks of 1024 nonzeros
 // of any kind, 16 workers x 4000 rows of 75 nonzeros, B = 200, took 93 us a
-// step; now 30 us (32 us with two waits a row in the margins and two LDS round
-// trips for each cold nonzero).
+// step; now 28 us (32 us with two waits a row in the margins and two LDS round
+// trips for each cold nonzero, 30 us with the table's chains from slot to slot).
 // U: nonzeros of a lane loaded together.
 template <int U>
 __device__ __forceinline__ void general_step(const SgdArgs& a, const Views& w, const RowInfo* ri, int Bp, Shared& sh,

@@ -161,7 +161,7 @@ __device__ __forceinline__ double row16_sum(double v) {
 // is read by one XCD, one worker at a time, and stays in its L2; nonzeros,
 // read once, are loaded non-temporally.  64 x 2^20, 4096 samples each of 83
 // nonzeros, a call: 488 us with samples of a block contiguous, 419 in this
-// order, 408 non-temporally, 389 with the loss out of line (below); a pass over
+// order, 408 non-temporally, 389 with the loss out of line (above); a pass over
 // the samples for each of the two models: 452.
 __global__ __launch_bounds__(256, 8) void loss_csr_kernel(MetricArgs a) {
   __shared__ double sh[256];
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256, 4) void loss_dense_kernel(MetricArgs a, int nc
   for (int64_t r = r0 + 4 * wave; r < r1; r += 16) {
     const float* x = a.X + (int64_t(i) * a.S + r) * a.ldx;
     double mo[4] = {0.0, 0.0, 0.0, 0.0}, mb[4] = {0.0, 0.0, 0.0, 0.0};
-    // columns c .. c + 3 of the four rows (the last row again past the chunk);
+    // columns c .. c + 3 of the four rows (past the chunk the first row again);
     // lanes past the last column read column 0 and are masked below.  Rows and
     // w_bar are padded to whole groups of four.
     auto load = [&](Cols& q, int64_t c) {

@@ -23,9 +23,10 @@
 // launch_mix_cols names): a workgroup takes all n rows of a narrow column range
 // through LDS, see mix_cols_kernel.
 //
-// tile kernel (n above 1024 and what the column kernel leaves): a tile is one 1 KiB segment of 16 consecutive output
-// rows, one wave per row segment with 16-byte loads; the tiles of one column
-// range go to one XCD so that re-reads of a neighbour's segment hit its L2.
+// tile kernel (n above 1024 and what the column kernel leaves): a tile is one
+// 1 KiB segment of 16 consecutive output rows, one wave per row segment with
+// 16-byte loads; the tiles of one column range go to one XCD so that re-reads of
+// a neighbour's segment hit its L2.
 //
 // Precision: the slab kernel accumulates its at most 17 terms with fp32
 // fused multiply-adds (error below 17 ulp of sum_j |P_ij w_j|); the tile and
